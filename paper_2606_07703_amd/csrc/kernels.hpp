@@ -62,6 +62,9 @@ hipError_t launch_sparse_block_mfma(const Prob &p, const void *q, const void *k,
 bool dense_mfma_supported(const Prob &p);
 hipError_t launch_dense_mfma(const Prob &p, const void *q, const void *k, const void *v,
                              void *o, float *lse, hipStream_t st);
+// Its kernels for the output of a chunk (qo > 0).
+hipError_t launch_dense_chunk_mfma(const Prob &p, const void *q, const void *k, const void *v,
+                                   void *o, float *lse, hipStream_t st);
 
 // Head-averaged mass with block aggregation.
 hipError_t launch_mass_rowwise(const Prob &p, const void *q, const void *k, const float *lse,

@@ -37,6 +37,7 @@ struct SupportKeys {
   static constexpr bool kLookup = true;   // rows are read from the LDS support cache
   static constexpr bool kBits = false;    // masked by position
   static constexpr bool kTable = false;
+  static constexpr bool kNaNs = false;
   int ntiles;
   const int *pos;
   const int *rows;

@@ -30,6 +30,7 @@ struct MaskedKeys {
   static constexpr bool kLookup = PAGED;   // rows are arithmetic, or read from the page table
   static constexpr bool kBits = true;
   static constexpr bool kTable = PAGED;
+  static constexpr bool kNaNs = true;   // rows that come out NaN are computed again
   int ntiles, steps;          // steps of a segment: a power of two
   int t0, nq, TQ;             // the workgroup's queries t0 .. t0 + nq - 1
   const int32_t *table;       // support rows of its KV head, one per b positions from qo

@@ -7,6 +7,8 @@
 * The persistent block-indexer work split (``csrc/persistent_units.hpp``)
   replayed over many sequence lengths, first groups and grid sizes: every
   (query group, key tile) unit is covered exactly once.
+* The kernels that look for NaN in their results: the device code of the build's
+  own flags holds no assumption that a value is not NaN.
 * The oracle's C source built with both sanitizers and run under the oracle
   pin tests.
 """
@@ -15,6 +17,8 @@ import subprocess
 import sys
 
 import pytest
+
+from paper_2606_07703_amd import build
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2606_07703_amd", "csrc")
@@ -52,6 +56,20 @@ def test_mass_grid_holds_every_item_once(tmp_path):
     exe = str(tmp_path / "mass_grid_cover")
     _gxx(exe, [os.path.join(NATIVE, "mass_grid_cover.cpp")])
     assert "grid ok" in _run(exe)
+
+
+@pytest.mark.parametrize("name", ["dense_chunk_mfma.hip", "sparse_mask_mfma.hip"])
+def test_kernels_that_look_for_nan_honour_it(tmp_path, name):
+    out = str(tmp_path / "dev.ll")
+    r = subprocess.run([build.HIPCC, *build.CFLAGS, *build.FILE_FLAGS.get(name, []),
+                        "--cuda-device-only", "-S", "-emit-llvm", "-Xclang", "-disable-llvm-passes",
+                        os.path.join(CSRC, name), "-o", out], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr
+    with open(out) as f:
+        text = f.read()
+    assert "amdgpu_kernel" in text
+    for assumed in (" nnan", "nofpclass(nan", '"no-nans-fp-math"="true"'):
+        assert assumed not in text, assumed
 
 
 def _runtime(name):
