@@ -135,6 +135,11 @@ typedef struct sp_problem {
  * computed (what the oracle needs). lse may be NULL. Both NULL is
  * SP_ERR_NULL. Fields used: seq_len, heads, head_dim, causal, dtype,
  * attn_scale.
+ * NaN and infinite entries of v: in fp32, and in bf16 with q_offset > 0, a
+ * row's outputs depend on v[0..t] alone. In bf16 with q_offset = 0 a weight of
+ * zero may still multiply such an entry after t, within the row's tile of
+ * 256/G queries (128/G at d = 256) or the 63 positions after it, and turn o[t,:]
+ * NaN in its dims; lse is not affected.
  */
 int sp_dense_attn(const sp_problem *p, const void *q, const void *k, const void *v,
                   void *o, float *lse, hipStream_t stream);

@@ -670,6 +670,73 @@ def test_dense_chunk_rows_do_not_see_later_values(S, qo, Hq, Hkv, d):
     assert not torch.isfinite(o2[at - qo:].float()).any()
 
 
+@pytest.mark.parametrize("S,qo,Hq,Hkv,d", [(1200, 700, 8, 2, 128), (1200, 700, 6, 2, 64),
+                                           (900, 100, 32, 2, 128), (700, 300, 4, 1, 256),
+                                           (33000, 32600, 4, 2, 64)])
+def test_dense_chunk_values_that_are_not_finite(S, qo, Hq, Hkv, d):
+    """Infinite and NaN values that a chunk's rows see give what they sum up to
+    in their dims and leave the others alone, with and without bad values after
+    the rows."""
+    say(f"dense, bad values S={S} q_offset={qo} {Hq}/{Hkv} d={d}")
+    inp = make_inputs(S, Hq, Hkv, d, dtype="bf16", seed=S, unit_v=True)
+    inf, nan = float("inf"), float("nan")
+    # (position, dim, value): dims 1 and 9 sum to one infinity, 5 to NaN, and 20
+    # turns NaN, 21 infinite, 22 and 9 NaN at positions within the chunk
+    at = (qo + S) // 2
+    bad = [(3, 1, inf), (qo - 1, 1, inf), (7, 5, nan), (40, 9, -inf), (at, 20, nan),
+           (at + 1, 21, inf), (at - 2, 22, inf), (at + 3, 22, -inf), (at + 3, 9, inf)]
+    v = inp.v.clone()
+    for s, dim, x in bad:
+        v[s, :, dim] = x
+    p = B.Problem(S, Hq, Hkv, d, q_offset=qo)
+    o = torch.empty(S - qo, Hq, d, dtype=torch.bfloat16, device="cuda")
+    B.sp_dense_attn(p, inp.q[qo:].contiguous().cuda(), inp.k.cuda(), v.cuda(), o, None)
+    torch.cuda.synchronize()
+    got = o.cpu().double().numpy()
+    rows = np.unique(np.r_[qo:qo + 4, at - 6:at + 7, S - 3:S])
+    clean = torch.where(torch.isfinite(v.float()), v.float(), 0.0).to(torch.bfloat16)
+    ref = oracle.dense(inp.q, inp.k, clean, rows=rows)[0]
+    ref_abs = oracle.dense(inp.q, inp.k, clean.abs(), rows=rows)[0]
+    got = got[rows - qo]
+    for i, t in enumerate(rows):
+        want = np.zeros(d)
+        for s, dim, x in bad:
+            if s <= t:
+                with np.errstate(invalid="ignore"):
+                    want[dim] += x
+        hit = want != 0
+        expect = np.broadcast_to(want[hit], got[i][:, hit].shape)
+        assert np.array_equal(got[i][:, hit], expect, equal_nan=True), t
+        got[i][:, hit], ref[i][:, hit], ref_abs[i][:, hit] = 0, 0, 0
+    check_attention(got, ref, ref_abs, "bf16")
+
+
+def test_dense_chunk_time_with_a_visible_nan_value():
+    """A NaN value before a chunk's rows costs a pass over the values, not a
+    recomputation of every row."""
+    say("dense, time with a visible NaN value")
+    S, qo, Hq, Hkv, d = 8192, 7168, 32, 8, 128
+    inp = make_inputs(S, Hq, Hkv, d, dtype="bf16", seed=1)
+    p = B.Problem(S, Hq, Hkv, d, q_offset=qo)
+    q, k, v = inp.q[qo:].contiguous().cuda(), inp.k.cuda(), inp.v.cuda()
+    o = torch.empty(S - qo, Hq, d, dtype=torch.bfloat16, device="cuda")
+    ms = []
+    for bad in (False, True):
+        if bad:
+            v[100] = float("nan")
+        best = float("inf")
+        for _ in range(4):
+            e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            e0.record()
+            B.sp_dense_attn(p, q, k, v, o, None)
+            e1.record()
+            torch.cuda.synchronize()
+            best = min(best, e0.elapsed_time(e1))
+        ms.append(best)
+    assert torch.isnan(o.float()).all()
+    assert ms[1] < 4 * ms[0], ms
+
+
 @pytest.mark.parametrize("S,qo,b,Hq,Hkv,d,k,shuffle", [
     # sizes the masked kernel takes: one tile, two groups on odd and even tile
     # counts, ragged queries, odd group sizes, entries not a multiple of 4 and
