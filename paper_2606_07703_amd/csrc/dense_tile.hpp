@@ -174,8 +174,9 @@ __device__ __forceinline__ void dense_value_kinds(int t0, int end, int j, int Hk
 }
 
 // SPLIT: see AttnPipe. CHUNK: the queries start at position qo (0 otherwise),
-// and the P V product takes the weights to 2^-18, where whole sequences round
-// them to bf16. A weight of zero still multiplies its V row, and an infinite
+// and the P V product takes the weights in fp32, as three bf16 parts, where
+// whole sequences round them to bf16: 1024 queries of 8192 keys, 32/8 heads, d =
+// 128, take 215 us so (two parts 174, one key at a time in fp32 3600). A weight of zero still multiplies its V row, and an infinite
 // entry its weight's two parts, so infinite and NaN V entries reach outputs that
 // they should not. Where a chunk's rows come out NaN although their weights are
 // numbers, the workgroup looks its values over: rows before the last such

@@ -711,6 +711,43 @@ def test_dense_chunk_values_that_are_not_finite(S, qo, Hq, Hkv, d):
     check_attention(got, ref, ref_abs, "bf16")
 
 
+@pytest.mark.parametrize("S,qo,d", [(1200, 700, 128), (9000, 8700, 128), (700, 100, 64),
+                                    (900, 300, 256)])
+def test_dense_chunk_weights_keep_fp32(S, qo, d):
+    """Weights 1, e^-x, 1 whose values cancel to 2^-17 of their size in the dim of
+    that x: what is left shows the weights' own error. fp32 weights (exp2 and its
+    argument a few 2^-24) leave less than 2^-20 of the values; a sum that
+    carries e^-x to 2^-18 leaves more in some of the rows."""
+    say(f"dense, weights of a chunk S={S} q_offset={qo} d={d}")
+    Hq, Hkv = 8, 2
+    rng = np.random.default_rng(S)
+    bf = lambda x: torch.from_numpy(np.asarray(x, dtype=np.float32)).to(torch.bfloat16)
+    f64 = lambda x: x.double().numpy()
+    x = f64(bf(rng.uniform(0.02, 1.5, d)))
+    q, k, v = np.zeros((S, Hq, d)), np.zeros((S, Hkv, d)), np.zeros((S, Hkv, d))
+    q[:, :, 2], k[:, :, 2] = 1.0, -300.0           # every key has no weight,
+    at = np.array([5, 70, qo - 1])
+    k[at, :, 2] = 0.0                              # but these three
+    dim = np.arange(S * Hq).reshape(S, Hq) % d
+    q[:, :, 1], k[at[1], :, 1] = -x[dim], 1.0
+    w = np.exp(-x)
+    for j in range(Hkv):
+        b = f64(bf(rng.uniform(1.0, 2.0, d)))
+        a = f64(bf(-w * b))
+        v[at[1], j], v[at[0], j], v[at[2], j] = b, a, f64(bf(-w * b - a))
+    p = B.Problem(S, Hq, Hkv, d, q_offset=qo, attn_scale=1.0)
+    o = torch.empty(S - qo, Hq, d, dtype=torch.bfloat16, device="cuda")
+    B.sp_dense_attn(p, bf(q[qo:]).cuda(), bf(k).cuda(), bf(v).cuda(), o, None)
+    torch.cuda.synchronize()
+    got = np.take_along_axis(f64(o.cpu()), dim[qo:, :, None], axis=2)[..., 0]
+    head = np.arange(Hq)[None] // (Hq // Hkv)
+    di = dim[qo:]
+    ref = ((v[at[0], head, di] + v[at[2], head, di] + w[di] * v[at[1], head, di])
+           / (2.0 + w[di]))
+    assert np.abs(ref).max() < 2.0 ** -16
+    assert np.abs(got - ref).max() < 2.0 ** -20
+
+
 def test_dense_chunk_time_with_a_visible_nan_value():
     """A NaN value before a chunk's rows costs a pass over the values, not a
     recomputation of every row."""
