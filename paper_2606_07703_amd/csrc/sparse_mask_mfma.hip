@@ -151,8 +151,10 @@ struct MaskLayout {
   static constexpr int BITS = TILES > 96 * 1024 ? 24 * 1024 : 64 * 1024;
   static constexpr int LDS = TILES + BITS;
   static constexpr int MIN_TQ = ROWS / 16;   // queries at the most heads a group
-  static constexpr int NF = 4;   // waves that compute NaN rows again
-  static_assert(LDS >= L::lds_bytes(true, NW) && LDS >= NF * (int)sizeof(QuerySlot<D>),
+  // waves that compute NaN rows again: as many as have their slots in the storage
+  static constexpr int NF_MAX = LDS / (int)sizeof(QuerySlots<D, 1>);
+  static constexpr int NF = NF_MAX < NW ? NF_MAX : NW;
+  static_assert(LDS >= L::lds_bytes(true, NW) && LDS >= (int)sizeof(QuerySlots<D, NF>),
                 "the output rows and the gather slots reuse the storage");
   static_assert(LDS + ROWS * 4 + BITS / MIN_TQ <= 160 * 1024, "fits the LDS of a CU");
   static_assert(2 * 8 * ROWS <= BITS, "two tiles' bits at one head per group");
@@ -214,11 +216,12 @@ __global__ __launch_bounds__(attn_max_waves<D>() * 64) SP_ATTN_OCCUPANCY(D) void
   drain_memory();   // this wave's rows are written before another wave rewrites them
   if (!__syncthreads_or(nan)) return;
   if (wave >= M::NF) return;
-  QuerySlot<D> *slots = reinterpret_cast<QuerySlot<D> *>(lds);
+  auto &slots = *reinterpret_cast<QuerySlots<D, M::NF> *>(lds);
   for (int i = wave; i < nq; i += M::NF)
     if (again[i])
       query_attend<D>(t0 + i, j, Hq, Hkv, G, kk, scale_log2, q, k, v,
-                      table + (size_t)((t0 + i - qo) / b) * kk, o, pages, slots[wave], lane);
+                      table + (size_t)((t0 + i - qo) / b) * kk, o, pages, slots.pos[wave],
+                      slots.rows[wave], lane);
 }
 
 template <int D, bool SPLIT>

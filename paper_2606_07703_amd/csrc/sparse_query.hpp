@@ -39,10 +39,15 @@ template <int D>
 struct QuerySlot {
   static constexpr int VRB = 2 * D + 32;   // V row bytes: conflict-free transpose reads
   static constexpr int KRB = 2 * D + 16;   // K row bytes: conflict-free operand reads
-  int pos[kPosChunk];
-  // a tile's K rows, then (once its products have read them) the same tile's
-  // V rows
-  char rows[kQT * (VRB > KRB ? VRB : KRB)];
+  // bytes of a tile's K rows, then (once its products have read them) of the
+  // same tile's V rows
+  static constexpr int ROWS = kQT * (VRB > KRB ? VRB : KRB);
+};
+// The LDS of NW waves.
+template <int D, int NW>
+struct QuerySlots {
+  int pos[NW][kPosChunk];
+  char rows[NW][QuerySlot<D>::ROWS];
 };
 
 template <class Op>
@@ -56,7 +61,8 @@ __device__ __forceinline__ float reduce4(float x, Op op) {
 }
 
 // q and o are addressed by position (the caller shifts them back by the chunk
-// start); row is query t's support row of kk entries for KV head j.
+// start); row is query t's support row of kk entries for KV head j; ipos and
+// rows are the wave's own (QuerySlots).
 template <int D>
 __device__ __forceinline__ void query_attend(int t, int j, int Hq, int Hkv, int G, int kk,
                                              float scale_log2, const uint16_t *__restrict__ q,
@@ -64,15 +70,14 @@ __device__ __forceinline__ void query_attend(int t, int j, int Hq, int Hkv, int 
                                              const uint16_t *__restrict__ v,
                                              const int32_t *__restrict__ row,
                                              uint16_t *__restrict__ o, KvPages pages,
-                                             QuerySlot<D> &sh, int lane) {
+                                             int *ipos, char *rows, int lane) {
   constexpr int KS = D / 32, DT = D / 16;
   constexpr int PPR = D / 8;         // 16-byte pieces per K/V row
   constexpr int RPL = PPR / 2;       // V pieces per lane per tile (8 rows x PPR / 16 lanes)
   constexpr int VRB = QuerySlot<D>::VRB, KRB = QuerySlot<D>::KRB;
   const int g = lane >> 4, c16 = lane & 15;
-  int *ipos = sh.pos;
-  char *vb = sh.rows;
-  char *kbs = sh.rows;
+  char *vb = rows;
+  char *kbs = rows;
 
   // Q as the B operand of S^T = K Q^T: column c16 is head j*G + c16.
   const bool hcol = c16 < G;
@@ -95,17 +100,23 @@ __device__ __forceinline__ void query_attend(int t, int j, int Hq, int Hkv, int 
     const int n = min(kPosChunk, kk - c0);
     // Copy the chunk of the support row into the wave's slot as K/V rows;
     // entries that cannot contribute (sentinel, out of range, after t, a
-    // page outside the cache) become -1. The tile loop ends after the last
-    // usable entry.
-    int last = -1;
+    // page outside the cache) become -1, and read the last of the usable rows
+    // in its place: their weight of zero must not meet a value row that the
+    // query does not attend to. The tile loop ends after the last usable
+    // entry.
+    int last = -1, top = -1;
     for (int e = lane; e < kPosChunk; e += 64) {
       int s = e < n ? row[c0 + e] : -1;
       s = (s >= 0 && s <= t) ? pages.row(s) : -1;
       ipos[e] = s;
       if (s >= 0) last = e;
+      top = max(top, s);
     }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) last = max(last, __shfl_xor(last, off, 64));
+    for (int off = 32; off > 0; off >>= 1) {
+      last = max(last, __shfl_xor(last, off, 64));
+      top = max(top, __shfl_xor(top, off, 64));
+    }
     const int ntiles = (last + kQT) / kQT;
     if (ntiles == 0) continue;
 
@@ -135,7 +146,7 @@ __device__ __forceinline__ void query_attend(int t, int j, int Hq, int Hkv, int 
           static_assert(PPR == 8, "d = 64, 128 or 256");
           s = c16 >= 8 ? ps[2 * e + 1] : ps[2 * e];
         }
-        const size_t rb = (size_t)max(s, 0) * kv_row + kv_head + vpiece(e) * 8;
+        const size_t rb = (size_t)min((uint32_t)s, (uint32_t)top) * kv_row + kv_head + vpiece(e) * 8;
         kreg[e] = ldg16(k + rb);
         vreg[e] = ldg16(v + rb);
       }

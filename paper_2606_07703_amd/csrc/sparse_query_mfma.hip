@@ -21,14 +21,15 @@ __global__ __launch_bounds__(NW * 64) void sparse_query_kernel(
     const uint16_t *__restrict__ v, const int32_t *__restrict__ idx,
     uint16_t *__restrict__ o, KvPages pages, int qo) {
   // q and o are addressed by position: the host shifts them back by qo rows
-  __shared__ __align__(16) QuerySlot<D> sh[NW];
+  __shared__ __align__(16) QuerySlots<D, NW> sh;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int j = blockIdx.x % Hkv;
   const int grp = n_groups - 1 - blockIdx.x / Hkv;   // longest queries first
   const int t = qo + grp * NW + wave;
   if (t >= S) return;   // no workgroup barrier below: waves are independent
   const int32_t *row = idx + (size_t)j * gstride + (size_t)((t - qo) / b) * kk;
-  query_attend<D>(t, j, Hq, Hkv, G, kk, scale_log2, q, k, v, row, o, pages, sh[wave], lane);
+  query_attend<D>(t, j, Hq, Hkv, G, kk, scale_log2, q, k, v, row, o, pages, sh.pos[wave],
+                  sh.rows[wave], lane);
 }
 
 template <int D>

@@ -439,7 +439,7 @@ def test_paged_sparse_attention(S, Hq, Hkv, d, b, dtype, ps, head_axis):
 def test_paged_head_dim_256_long_support(k_):
     """At head_dim 256 the paged block kernel caches supports of up to 2048
     entries (its K/V tiles fill most of LDS); a longer support takes the
-    row-wise kernel. Both match the contiguous call, which is held to the
+    kernels of per-query supports (here the masked tiles). Both match the contiguous call, which is held to the
     oracle on sampled rows of sharp inputs (32 key tiles, rescale after the
     first)."""
     S, Hq, Hkv, d, b = 2300, 8, 2, 256, 64
@@ -460,7 +460,7 @@ def test_paged_head_dim_256_long_support(k_):
     check_attention(o_c.cpu().double().numpy()[rows], ref, ref_abs, "bf16", "contiguous: ")
     if k_ <= 2048:
         assert torch.equal(o, o_c)
-    else:   # row-wise (paged) against the block kernel (contiguous)
+    else:   # masked tiles (paged) against the block kernel (contiguous)
         check_attention(o.cpu().double().numpy()[rows], ref, ref_abs, "bf16", "paged: ")
 
 
@@ -849,6 +849,94 @@ def test_unselected_value_rows_may_hold_anything():
     args = [oracle.sparse(inp.q, inp.k, x, table, 1) for x in (inp.v, inp.v.abs())]
     for o in out:
         check_attention(o.double().numpy(), *args, "bf16")
+
+
+# S, q_offset, block_q, Hq, Hkv, d, k, page size: shapes the masked kernel takes, with the keys split between wave
+# groups and not, at each head dim, odd and even tile counts, a lone tile,
+# several mask segments, chunks, pages smaller than, equal to and astride a tile
+MASKED = [
+    (64, 0, 1, 64, 32, 128, 64, 16), (65, 0, 1, 192, 32, 64, 64, 7),
+    (300, 0, 1, 24, 8, 128, 299, 1), (449, 120, 4, 48, 16, 64, 401, 64),
+    (449, 120, 1, 128, 8, 64, 448, 7), (2500, 0, 1, 16, 16, 64, 1500, 16),
+    (700, 0, 1, 128, 32, 64, 466, 16), (1100, 0, 1, 96, 32, 128, 733, 64),
+    (1500, 0, 1, 64, 16, 128, 1000, 48), (300, 0, 1, 32, 8, 256, 299, 16),
+    (560, 200, 2, 48, 16, 256, 500, 7),
+]
+
+
+def _cache(k, v, ps, seed):
+    """K and V on scattered pages of a cache that is NaN elsewhere, its first row
+    among it, and the page table, with one entry outside the cache."""
+    S = k.shape[0]
+    n = -(-S // ps)
+    pt = 1 + np.random.default_rng(seed).permutation(n + 2)[:n].astype(np.int32)
+    pages = []
+    for x in (k, v):
+        full = torch.zeros((n * ps,) + tuple(x.shape[1:]), dtype=x.dtype)
+        full[:S] = x
+        c = torch.full((n + 3, ps) + tuple(x.shape[1:]), float("nan"), dtype=x.dtype)
+        c[torch.from_numpy(pt).long()] = full.view(n, ps, *x.shape[1:])
+        pages.append(c)
+    if n > 2:
+        pt[n // 2] = n + 100
+    return pages[0], pages[1], torch.from_numpy(pt)
+
+
+def _masked_run(p, inp, v, table, ps, seed):
+    """The contiguous call (ps = 0) or the paged one, and the positions it sees."""
+    o = torch.full((p.num_queries, p.num_q_heads, p.head_dim), 7.0, dtype=torch.bfloat16,
+                   device="cuda")
+    q = inp.q[p.q_offset:].contiguous().cuda()
+    there = torch.ones(p.seq_len, dtype=torch.bool)
+    if ps:
+        kp, vp, pt = _cache(inp.k, v, ps, seed)
+        at = torch.arange(p.seq_len) // ps
+        there = (pt.long()[at] >= 0) & (pt.long()[at] < kp.shape[0])
+        B.sp_sparse_gqa_attn_paged(p, q, kp.cuda(), vp.cuda(), pt.cuda(), table.cuda(), o)
+    else:
+        B.sp_sparse_gqa_attn(p, q, inp.k.cuda(), v.cuda(), table.cuda(), o)
+    torch.cuda.synchronize()
+    return o.cpu(), there
+
+
+def _masked_check(p, inp, o, table, there):
+    S, qo, b = p.seq_len, p.q_offset, p.block_q
+    at = np.unique(np.concatenate([np.arange(qo, S, max(1, (S - qo) // 60)), [S - 1]]))
+    whole = torch.full((-(-S // b), p.topk), -1, dtype=torch.int32)
+    ok = (table >= 0) & (table < S)
+    ok &= there[table.clamp(0, S - 1).long()]
+    whole[qo // b:] = torch.where(ok, table, torch.full_like(table, -1))
+    check_attention(o.double().numpy()[at - qo],
+                    oracle.sparse(inp.q, inp.k, inp.v, whole, b, rows=at),
+                    oracle.sparse(inp.q, inp.k, inp.v.abs(), whole, b, rows=at), "bf16")
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("S,qo,b,Hq,Hkv,d,k,ps", MASKED)
+def test_masked_tiles_and_pages(S, qo, b, Hq, Hkv, d, k, ps, paged):
+    say(f"masked S={S} q_offset={qo} b={b} {Hq}/{Hkv} d={d} k={k} page={ps if paged else 0}")
+    inp = make_inputs(S, Hq, Hkv, d, dtype="bf16", seed=S + k, peaked=True, unit_v=True,
+                      k_ramp=4.0)
+    rows = list(range(qo // b, (S + b - 1) // b)) if qo else None
+    table = make_support(S, b, k, seed=k, shuffle=True, random_rows=rows)[qo // b:].clone()
+    table[1::5, ::11] = S + 5                      # out of range
+    p = B.Problem(S, Hq, Hkv, d, topk=k, block_q=b, q_offset=qo)
+    o, there = _masked_run(p, inp, inp.v, table, ps * paged, S)
+    _masked_check(p, inp, o, table, there)
+    # bad value rows: queries that select none of them keep their outputs
+    v = inp.v.clone()
+    v[3::34], v[20::34] = float("nan"), float("-inf")
+    bad = torch.zeros(S, dtype=torch.bool)
+    bad[3::17] = True
+    o2, _ = _masked_run(p, inp, v, table, ps * paged, S)
+    for t in range(qo, S, max(1, (S - qo) // 200)):
+        row = table[(t - qo) // b].long()
+        row = row[(row >= 0) & (row <= t)]
+        row = row[there[row]]
+        if not bad[row].any():
+            assert (o2[t - qo].float() - o[t - qo].float()).abs().max() <= 2e-2, t
+        else:
+            assert not torch.isfinite(o2[t - qo].float()).all(), t
 
 
 # ------------------------------------------------------ d = d_idx = 256 (f3)
