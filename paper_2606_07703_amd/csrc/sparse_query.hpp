@@ -31,6 +31,7 @@ namespace sp {
 
 constexpr int kQT = 32;         // support entries per tile
 constexpr int kPosChunk = 2048; // support entries held in LDS at a time
+constexpr int kPosStep = 512;   // ... of which this many are copied at a time
 constexpr float kLazyQ = 8.f;   // running max may lag by up to 2^8
 
 typedef short qv4i16 __attribute__((ext_vector_type(4)));
@@ -105,12 +106,16 @@ __device__ __forceinline__ void query_attend(int t, int j, int Hq, int Hkv, int 
     // query does not attend to. The tile loop ends after the last usable
     // entry.
     int last = -1, top = -1;
-    for (int e = lane; e < kPosChunk; e += 64) {
-      int s = e < n ? row[c0 + e] : -1;
-      s = (s >= 0 && s <= t) ? pages.row(s) : -1;
-      ipos[e] = s;
-      if (s >= 0) last = e;
-      top = max(top, s);
+    for (int e0 = 0; e0 < n; e0 += kPosStep) {
+#pragma unroll
+      for (int u = 0; u < kPosStep / 64; ++u) {
+        const int e = e0 + u * 64 + lane;
+        int s = e < n ? row[c0 + e] : -1;
+        s = (s >= 0 && s <= t) ? pages.row(s) : -1;
+        ipos[e] = s;
+        if (s >= 0) last = e;
+        top = max(top, s);
+      }
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
