@@ -48,8 +48,7 @@ hipError_t launch_sparse_query_mfma(const Prob &p, const void *q, const void *k,
                                     const int32_t *idx, void *o, hipStream_t st,
                                     KvPages pages = KvPages());
 // Per-query supports by masking every key before the query instead of
-// gathering the selected ones, and where that pays.
-bool sparse_mask_pays(const Prob &p);
+// gathering the selected ones, where that pays (sparse_mask_pays).
 hipError_t launch_sparse_mask_mfma(const Prob &p, const void *q, const void *k, const void *v,
                                    const int32_t *idx, void *o, hipStream_t st, KvPages pages);
 // paged: K/V read through a page table (a smaller support fits LDS at d = 256)

@@ -230,13 +230,13 @@ hipError_t launch_t(const Prob &p, const void *q, const void *k, const void *v,
   using M = MaskLayout<D, SPLIT>;
   const int TQ = M::ROWS / p.G;
   const int nqt = (p.nq + TQ - 1) / TQ;
-  int seg_tiles = 2;   // the most whose bits fit, a power of two
-  while (2 * seg_tiles * 8 * TQ <= M::BITS) seg_tiles *= 2;
+  const MaskShape m = mask_shape(p);   // (m.split == SPLIT)
+  static_assert(M::BITS == 64 * 1024 || M::BITS == 24 * 1024, "as in mask_shape");
   const size_t shift = (size_t)p.qo * p.Hq * D;   // chunk rows addressed by position
 #define SP_MASKED(PAGED)                                                                       \
   hipLaunchKernelGGL((sparse_mask_kernel<D, SPLIT, PAGED>), dim3(nqt * p.Hkv), dim3(M::NW * 64), \
                      0, st, p.S, p.qo, p.Hq, p.Hkv, p.G, p.b, p.k, p.idx_group_stride(), TQ,   \
-                     nqt, seg_tiles, p.scale * kLog2e, (const uint16_t *)q - shift,            \
+                     nqt, m.seg_tiles(p), p.scale * kLog2e, (const uint16_t *)q - shift,        \
                      (const uint16_t *)k, (const uint16_t *)v, idx, (uint16_t *)o - shift, pages)
   if (pages.table)
     SP_MASKED(true);
@@ -250,54 +250,11 @@ template <int D>
 hipError_t launch_d(const Prob &p, const void *q, const void *k, const void *v,
                     const int32_t *idx, void *o, hipStream_t st, KvPages pages) {
   if constexpr (D <= 128)
-    if (few_workgroups(p, attn_max_waves<D>() * kAttnQPW / p.G))
-      return launch_t<D, true>(p, q, k, v, idx, o, st, pages);
+    if (mask_shape(p).split) return launch_t<D, true>(p, q, k, v, idx, o, st, pages);
   return launch_t<D, false>(p, q, k, v, idx, o, st, pages);
 }
 
 }  // namespace
-
-// Estimates of both kernels' times in us, fitted to their measured times over
-// sequences of 1K to 32K tokens and their last 1K rows, k 128 to 2048, 1 to 16
-// heads a group:
-//   gather: per selected row and KV head 12 / 24.5 / 73 ps at d = 64 / 128 /
-//     256, per query and KV head 1.2 / 2.3 / 2.3 ns;
-//   masked: 1.55 / 2.1 / 2.8 us for a 64-key step of 256 query rows (128 at d
-//     = 256), 1.3 times that for a split step, times the longest workgroup's
-//     steps or the even share of all of them; filling the masks 0.5 ns per
-//     entry and CU for every segment whose pieces meet it (all 512 entries of
-//     a wave's pieces are skipped together).
-// The line is the same for a paged cache, whose masked steps are up to 1.25
-// times as long, hence the factor (and the two agree to the bit).
-// Gathered / masked: 4096 tokens, 16/4 heads, d = 128, k = 512: 246 / 101 us;
-// 8192, 32/8, k = 1024: 1512 / 594; 32768, 32/8, k = 2048: 15.7 / 9.5 ms; on the
-// other side 1024 rows at 15360, 32/8, k = 1024: 226 / 326 us; 8192 tokens at
-// 16/2 heads, k = 512: 242 / 293.
-bool sparse_mask_pays(const Prob &p) {
-  constexpr double kCus = 256;
-  const double S = p.S, qo = p.qo, nq = p.nq, k = p.k, Hkv = p.Hkv;
-  const int dx = p.d == 64 ? 0 : p.d == 128 ? 1 : 2;
-  const double cut = k < qo ? 0 : (k < S ? k : S) - qo;   // rows that see fewer than k keys
-  const double entries = nq * k - cut * (k - qo - 0.5 * cut);
-  static const double kRow[3] = {12e-6, 24.5e-6, 73e-6}, kQuery[3] = {1.2e-3, 2.3e-3, 2.3e-3};
-  const double gather = Hkv * (entries * kRow[dx] + nq * kQuery[dx]);
-  static const double kStep[3] = {1.55, 2.1, 2.8};
-  int rows = p.d == 256 ? 128 : 256;
-  const bool split = p.d != 256 && few_workgroups(p, rows / p.G);
-  const int bits = p.d == 64 || (p.d == 128 && !split) ? 64 * 1024 : 24 * 1024;
-  if (split) rows = 128;
-  const int TQ = rows / p.G;
-  int seg_tiles = 2;
-  while (2 * seg_tiles * 8 * TQ <= bits) seg_tiles *= 2;
-  const double longest = (S + 63) / 64, mean = (qo + S) / 128;
-  const double share = ((p.nq + TQ - 1) / TQ) * Hkv * mean / kCus;
-  const double steps = (longest > share ? longest : share) * (split ? 0.5 : 1.0);
-  const double segs = 0.5 + mean / seg_tiles > 1 ? 0.5 + mean / seg_tiles : 1;
-  const double scans = segs < 1 + segs * 512 / k ? segs : 1 + segs * 512 / k;
-  const double masked =
-      steps * kStep[dx] * (split ? 1.3 : 1.0) + 0.5e-3 * entries * Hkv * scans / kCus;
-  return 1.2 * masked < gather;
-}
 
 hipError_t launch_sparse_mask_mfma(const Prob &p, const void *q, const void *k, const void *v,
                                    const int32_t *idx, void *o, hipStream_t st, KvPages pages) {

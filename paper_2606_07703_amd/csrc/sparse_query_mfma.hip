@@ -9,6 +9,7 @@
 //
 // Where the supports cover enough of the keys before them, multiplying every
 // key and masking costs less than gathering (launch_sparse_mask_mfma).
+#include "attn_rules.hpp"
 #include "sparse_query.hpp"
 
 namespace sp {

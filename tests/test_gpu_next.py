@@ -851,7 +851,8 @@ def test_unselected_value_rows_may_hold_anything():
         check_attention(o.double().numpy(), *args, "bf16")
 
 
-# S, q_offset, block_q, Hq, Hkv, d, k, page size: shapes the masked kernel takes, with the keys split between wave
+# S, q_offset, block_q, Hq, Hkv, d, k, page size: shapes the masked kernel takes
+# (test_host_native.py holds the rule to that), with the keys split between wave
 # groups and not, at each head dim, odd and even tile counts, a lone tile,
 # several mask segments, chunks, pages smaller than, equal to and astride a tile
 MASKED = [

@@ -58,6 +58,31 @@ def test_mass_grid_holds_every_item_once(tmp_path):
     assert "grid ok" in _run(exe)
 
 
+def test_masked_shapes_take_the_masked_kernel(tmp_path):
+    """The shapes of the masked kernel's GPU tests are on its side of the rule, in
+    both of its forms, and calls it was measured slower at are not."""
+    from test_gpu_next import MASKED
+    exe = str(tmp_path / "mask_rule")
+    _gxx(exe, [os.path.join(NATIVE, "mask_rule.cpp")])
+
+    def rule(shapes):
+        text = "\n".join(" ".join(map(str, s)) for s in shapes)
+        r = subprocess.run([exe], input=text, capture_output=True, text=True, timeout=60)
+        assert r.returncode == 0, r.stderr
+        return [tuple(map(int, ln.split())) for ln in r.stdout.splitlines()]
+
+    taken = [s[:2] + s[3:7] for s in MASKED]
+    got = rule(taken)
+    assert len(got) == len(taken) and all(m for m, _ in got), list(zip(taken, got))
+    assert {(s[4], split) for s, (_, split) in zip(taken, got)} == {
+        (64, 0), (64, 1), (128, 0), (128, 1), (256, 0)}
+    # 1024 queries at one head a group: 299 us against 219 gathered; rows of 64
+    # entries; a support row too long to count in 32 bits
+    gathered = [(4096, 3072, 8, 8, 128, 1024), (4096, 3072, 8, 8, 128, 2048),
+                (2048, 0, 32, 8, 128, 64), (64, 0, 1, 1, 64, 2_000_000_000)]
+    assert not any(m for m, _ in rule(gathered))
+
+
 @pytest.mark.parametrize("name", ["dense_chunk_mfma.hip", "sparse_mask_mfma.hip"])
 def test_kernels_that_look_for_nan_honour_it(tmp_path, name):
     out = str(tmp_path / "dev.ll")
