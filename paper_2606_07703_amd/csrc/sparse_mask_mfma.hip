@@ -11,6 +11,14 @@
 // segment's first step the workgroup clears the bits and sets those of its
 // queries' support entries (any order, entries out of [0, t] dropped).
 //
+// The line between the two kernels is drawn for full support rows. Rows may hold
+// sentinels instead: a workgroup whose queries have so few usable entries that
+// gathering them takes less than its key tiles finds that in its first fill of
+// the bits, or after a part of it, and gathers. Tables of k = 2048 with 16
+// entries each, 32768 tokens, 32/8 heads, d = 128: 9.4 -> 2.4 ms (2.05 by the
+// gather kernel); k = 512 with 16, 4096 tokens, 16/4: 110 -> 71 us (73); at d = 64,
+// k = 1024 with 16, only 93 -> 91 (59), as most of that is the fill.
+//
 // A weight of zero still multiplies its V row, so an infinite or NaN V entry
 // that no query selects would turn outputs to NaN. Rows that come out NaN are
 // therefore computed again from the selected rows alone (query_attend).
@@ -40,6 +48,8 @@ struct MaskedKeys {
   KvPages pages;
   int S;
   uint2 *paged;               // PAGED: the segment's keys on a page of the cache
+  int *seen;                  // usable entries, a quarter of them looked at
+  int few;                    // so many or fewer are gathered (-1: none)
 
   // a tile past the last (see AttnPipe::tile; its bits are clear) takes the
   // last one's rows
@@ -68,6 +78,10 @@ struct MaskedKeys {
     }
     return r;
   }
+  // After the first fill: whether to gather (the same for the whole workgroup).
+  __device__ __forceinline__ bool leave() const {
+    return __builtin_amdgcn_readfirstlane(*seen) * 4 <= few;
+  }
   // Bits of the segment that starts at key tile tile0. (query, 8-entry piece)
   // items, two of a thread's in flight; entries of a piece that share a word
   // (neighbours of an ascending row) are merged before the LDS atomic.
@@ -91,8 +105,10 @@ struct MaskedKeys {
     const int kc = (kk + 7) / 8, items = nq * kc;
     const bool vec = (kk & 3) == 0;   // every row starts 16-byte aligned
     constexpr int U = 2;
+    int usable = 0;
 #pragma unroll 1
-    for (int i0 = tid; i0 < items; i0 += U * NT) {
+    for (int base = 0; base < items; base += U * NT) {
+      const int i0 = base + tid;
       int e[U][8], qq[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -115,6 +131,7 @@ struct MaskedKeys {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int t = t0 + qq[u];
+        usable += (e[u][0] >= 0 && e[u][0] <= t) + (e[u][4] >= 0 && e[u][4] <= t);
         // ascending rows: most pieces of a wave lie wholly outside the segment
         bool some = false;
 #pragma unroll
@@ -136,8 +153,25 @@ struct MaskedKeys {
           if (!carry && w[x] >= 0) atomicOr(&words[w[x]], bit[x]);
         }
       }
+      // the entries looked at so far may be few enough to leave at once (where
+      // the fill is long: the wait takes 3 us of the 4 that a short one does)
+      if (tile0 == 0 && base == 0 && items >= 8 * U * NT && few >= 0) {
+        tally(usable);
+        usable = 0;
+        __syncthreads();
+        const bool gone =
+            __builtin_amdgcn_readfirstlane(*seen) * 4 <= few * ((float)(U * NT / 2) / items);
+        __syncthreads();   // every wave has read it
+        if (gone) return;
+      }
     }
+    if (tile0 == 0) tally(usable);
     __syncthreads();
+  }
+  __device__ __forceinline__ void tally(int n) const {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) n += __shfl_xor(n, off, 64);
+    if ((threadIdx.x & 63) == 0) atomicAdd(seen, n);
   }
 };
 
@@ -163,15 +197,17 @@ struct MaskLayout {
 template <int D, bool SPLIT, bool PAGED>
 __global__ __launch_bounds__(attn_max_waves<D>() * 64) SP_ATTN_OCCUPANCY(D) void sparse_mask_kernel(
     int S, int qo, int Hq, int Hkv, int G, int b, int kk, size_t gstride, int TQ, int nqt,
-    int seg_tiles, float scale_log2, const uint16_t *__restrict__ q,
-    const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
-    const int32_t *__restrict__ idx, uint16_t *__restrict__ o, KvPages pages) {
+    int seg_tiles, float tile_entries, float query_entries, float scale_log2,
+    const uint16_t *__restrict__ q, const uint16_t *__restrict__ k,
+    const uint16_t *__restrict__ v, const int32_t *__restrict__ idx,
+    uint16_t *__restrict__ o, KvPages pages) {
   // q and o are addressed by position: the host shifts them back by qo rows
   using M = MaskLayout<D, SPLIT>;
   constexpr int kNW = M::NW, NT = kNW * 64;
   __shared__ __align__(16) char lds[M::LDS];
   __shared__ uint2 paged[PAGED ? M::BITS / (8 * M::MIN_TQ) : 1];
   __shared__ int again[M::ROWS];   // queries to compute from their selected rows
+  __shared__ int seen;
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int h = lane >> 5, n = lane & 31;
@@ -187,38 +223,50 @@ __global__ __launch_bounds__(attn_max_waves<D>() * 64) SP_ATTN_OCCUPANCY(D) void
   QRow<D> qr;
   load_q_row<D>(q, Hq, G, j, t0, row0 + n, nrows, h, qr);
   if (tid < nq) again[tid] = 0;
+  if (tid == 0) seen = 0;
   AttnState<D> st;
   const uint32_t bits_a =
       (uint32_t)(size_t)(__attribute__((address_space(3))) char *)(lds + M::TILES);
-  const MaskedKeys<NT, SPLIT, PAGED> keys{tl / kAttnKT + 1, SPLIT ? seg_tiles / 2 : seg_tiles,
+  // entries that take as long to gather as the key tiles to multiply, at most
+  // three quarters of what full rows hold
+  const int ntiles = tl / kAttnKT + 1;
+  const float worth = ntiles * tile_entries - nq * query_entries;
+  const float most = 0.75f * nq * min(t0 + 1, kk);
+  const int few = worth <= 0.f ? -1 : (int)(worth < most ? worth : most);
+  const MaskedKeys<NT, SPLIT, PAGED> keys{ntiles, SPLIT ? seg_tiles / 2 : seg_tiles,
                                           t0, nq, TQ, table, qo, b, kk,
                                           reinterpret_cast<uint32_t *>(lds + M::TILES),
-                                          bits_a + (uint32_t)(qr.t - t0) * 8, pages, S, paged};
+                                          bits_a + (uint32_t)(qr.t - t0) * 8, pages, S, paged,
+                                          &seen, few};
   const int kv_rows = PAGED ? pages.num_pages * pages.page_size : S;
   AttnPipe<D, kNW, true, MaskedKeys<NT, SPLIT, PAGED>, SPLIT> pipe(lds, keys, k, v, kv_rows, Hkv,
                                                                    j, scale_log2, 0, qr, st);
   pipe.run();
-  if constexpr (SPLIT) {
-    attn_merge<D, true>(st, wave, lane, lds);
-    if (wave >= 4) qr.valid = false;   // group 0 writes the rows
-  }
-  // NaN by bit pattern, on values the compiler knows nothing about
-  uint32_t top = 0;
+  const bool left = keys.leave();
+  bool nan = false;
+  if (!left) {
+    if constexpr (SPLIT) {
+      attn_merge<D, true>(st, wave, lane, lds);
+      if (wave >= 4) qr.valid = false;   // group 0 writes the rows
+    }
+    // NaN by bit pattern, on values the compiler knows nothing about
+    uint32_t top = 0;
 #pragma unroll
-  for (int dt = 0; dt < AttnLayout<D>::DT; ++dt) {
-    settle(st.o[dt]);
+    for (int dt = 0; dt < AttnLayout<D>::DT; ++dt) {
+      settle(st.o[dt]);
 #pragma unroll
-    for (int e = 0; e < 16; ++e) top = max(top, __float_as_uint(st.o[dt][e]) & 0x7fffffffu);
+      for (int e = 0; e < 16; ++e) top = max(top, __float_as_uint(st.o[dt][e]) & 0x7fffffffu);
+    }
+    nan = qr.valid && top > 0x7f800000u;
+    attn_finish<D>(st, qr, Hq, o, nullptr, h, lds);
+    if (nan) again[qr.t - t0] = 1;
+    drain_memory();   // this wave's rows are written before another wave rewrites them
   }
-  const bool nan = qr.valid && top > 0x7f800000u;
-  attn_finish<D>(st, qr, Hq, o, nullptr, h, lds);
-  if (nan) again[qr.t - t0] = 1;
-  drain_memory();   // this wave's rows are written before another wave rewrites them
-  if (!__syncthreads_or(nan)) return;
+  if (!__syncthreads_or(nan || left)) return;
   if (wave >= M::NF) return;
   auto &slots = *reinterpret_cast<QuerySlots<D, M::NF> *>(lds);
   for (int i = wave; i < nq; i += M::NF)
-    if (again[i])
+    if (left || again[i])
       query_attend<D>(t0 + i, j, Hq, Hkv, G, kk, scale_log2, q, k, v,
                       table + (size_t)((t0 + i - qo) / b) * kk, o, pages, slots.pos[wave],
                       slots.rows[wave], lane);
@@ -232,11 +280,19 @@ hipError_t launch_t(const Prob &p, const void *q, const void *k, const void *v,
   const int nqt = (p.nq + TQ - 1) / TQ;
   const MaskShape m = mask_shape(p);   // (m.split == SPLIT)
   static_assert(M::BITS == 64 * 1024 || M::BITS == 24 * 1024, "as in mask_shape");
+  // a workgroup that gathers does so with NF waves, where the gather kernel has
+  // 12 / 8 / 6 on a CU at d = 64 / 128 / 256
+  constexpr double kCus = 256, kWaves = (D == 64 ? 12.0 : D == 128 ? 8.0 : 6.0) / M::NF;
+  const SparseRates r = sparse_rates(p);
+  const float tile_entries = (float)(r.step * (SPLIT ? 0.5 * kSplitStep : 1.0) /
+                                     (1.15 * kCus * kWaves * r.row)),
+              query_entries = (float)(r.query / r.row);
   const size_t shift = (size_t)p.qo * p.Hq * D;   // chunk rows addressed by position
 #define SP_MASKED(PAGED)                                                                       \
   hipLaunchKernelGGL((sparse_mask_kernel<D, SPLIT, PAGED>), dim3(nqt * p.Hkv), dim3(M::NW * 64), \
                      0, st, p.S, p.qo, p.Hq, p.Hkv, p.G, p.b, p.k, p.idx_group_stride(), TQ,   \
-                     nqt, m.seg_tiles(p), p.scale * kLog2e, (const uint16_t *)q - shift,        \
+                     nqt, m.seg_tiles(p), tile_entries, query_entries, p.scale * kLog2e,         \
+                     (const uint16_t *)q - shift,                                             \
                      (const uint16_t *)k, (const uint16_t *)v, idx, (uint16_t *)o - shift, pages)
   if (pages.table)
     SP_MASKED(true);

@@ -940,6 +940,34 @@ def test_masked_tiles_and_pages(S, qo, b, Hq, Hkv, d, k, ps, paged):
             assert not torch.isfinite(o2[t - qo].float()).all(), t
 
 
+@pytest.mark.parametrize("kind", ["none", "few", "half", "first"])
+@pytest.mark.parametrize("S,qo,b,Hq,Hkv,d,k,ps", [MASKED[3], MASKED[6], MASKED[7], MASKED[9],
+                                                  (3000, 0, 1, 64, 16, 128, 1024, 16)])
+def test_masked_tiles_of_rows_with_sentinels(S, qo, b, Hq, Hkv, d, k, ps, kind):
+    """Rows with no, few or in part few entries, which workgroups gather; the last
+    shape's masks take long enough to stop within the first fill."""
+    say(f"masked, {kind} entries S={S} q_offset={qo} b={b} {Hq}/{Hkv} d={d} k={k}")
+    inp = make_inputs(S, Hq, Hkv, d, dtype="bf16", seed=S + k, peaked=True, unit_v=True)
+    rows = list(range(qo // b, (S + b - 1) // b)) if qo else None
+    table = make_support(S, b, k, seed=k, shuffle=True, random_rows=rows)[qo // b:].clone()
+    n = table.shape[0]
+    if kind == "none":
+        table[:] = -1
+    elif kind == "few":
+        table[:, :-5] = -1                         # at the end of the row
+    elif kind == "half":
+        table[n // 2:, 9:] = -1
+    else:   # the first rows of every sixteen are full
+        keep = torch.arange(n) % 16 < 4
+        table[~keep, 2:] = -1
+    p = B.Problem(S, Hq, Hkv, d, topk=k, block_q=b, q_offset=qo)
+    for page in (0, ps):
+        o, there = _masked_run(p, inp, inp.v, table, page, S)
+        if kind == "none":
+            assert not o.float().any()
+        _masked_check(p, inp, o, table, there)
+
+
 # ------------------------------------------------------ d = d_idx = 256 (f3)
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_head_dim_256(dtype):

@@ -71,7 +71,7 @@ def test_masked_shapes_take_the_masked_kernel(tmp_path):
         assert r.returncode == 0, r.stderr
         return [tuple(map(int, ln.split())) for ln in r.stdout.splitlines()]
 
-    taken = [s[:2] + s[3:7] for s in MASKED]
+    taken = [s[:2] + s[3:7] for s in MASKED] + [(3000, 0, 64, 16, 128, 1024)]
     got = rule(taken)
     assert len(got) == len(taken) and all(m for m, _ in got), list(zip(taken, got))
     assert {(s[4], split) for s, (_, split) in zip(taken, got)} == {
