@@ -23,6 +23,7 @@
 // streams longer rows from memory on every pass, 512 threads a row.
 #include "common.hpp"
 #include "kernels.hpp"
+#include "topk_rules.hpp"
 
 namespace sp {
 namespace {
@@ -119,9 +120,7 @@ __device__ __forceinline__ int row_of(int i, int n) {
 }
 
 // ------------------------------------------------------------ register rows
-constexpr int kRegNT = 512;                   // most threads per row
-constexpr int kRun = 16;                      // consecutive positions per run
-constexpr int kRegSub = 4;                    // runs per thread
+constexpr int kRegNT = 512;                        // most threads per row
 constexpr int kRegCap = kRegNT * kRun * kRegSub;   // 32768 candidates
 // The first digit's histogram has kCopies interleaved copies, lane l counting
 // into copy l % kCopies: block-aggregated scores crowd into a few top bins,
@@ -647,25 +646,14 @@ void launch_reg_nt(const Prob &p, bool packed, const float *scores, int32_t *idx
                        p.W, scores, idx);
 }
 
-// Threads per row. Most of a row's time is the passes' fixed part (clearing and
-// scanning the bins, barriers), which fewer threads share out over more rows
-// on a CU: per-query rows with 64 / 256 / 512 threads, in us: 2048 rows of 2048
-// keys 19.5 / 22.8 / 33.5, 4096 of 4096 25.9 / 39.8 / 62.2; with 128 / 256 / 512:
-// 8192 rows of 8192 keys 71.5 / 83.6 / 123; with 256 / 512: 16384 rows of 16384
-// keys 214 / 299, 1024 of 16384 21.2 / 25.7, 512 of 512 12.2 / 13.6. Too few rows
-// to fill the CUs finish sooner with more threads: 64 rows of 4096 keys 18.7 /
-// 10.8 / 10.8 (64 / 256 / 512), 256 of 16384 15.2 / 12.1 (256 / 512).
 void launch_reg(const Prob &p, int ncmax, bool packed, const float *scores, int32_t *idx,
                 hipStream_t st) {
-  const int n = p.R * (p.ha ? p.Hkv : 1);
-  if (ncmax <= 64 * kRun * kRegSub && n >= 1536)
-    launch_reg_nt<64>(p, packed, scores, idx, st);
-  else if (ncmax <= 128 * kRun * kRegSub && n >= 2048)
-    launch_reg_nt<128>(p, packed, scores, idx, st);
-  else if (ncmax <= 256 * kRun * kRegSub && n >= 512)
-    launch_reg_nt<256>(p, packed, scores, idx, st);
-  else
-    launch_reg_nt<512>(p, packed, scores, idx, st);
+  switch (topk_threads(p, ncmax)) {
+    case 64: return launch_reg_nt<64>(p, packed, scores, idx, st);
+    case 128: return launch_reg_nt<128>(p, packed, scores, idx, st);
+    case 256: return launch_reg_nt<256>(p, packed, scores, idx, st);
+    default: return launch_reg_nt<512>(p, packed, scores, idx, st);
+  }
 }
 
 }  // namespace

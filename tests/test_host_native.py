@@ -58,29 +58,47 @@ def test_mass_grid_holds_every_item_once(tmp_path):
     assert "grid ok" in _run(exe)
 
 
+def _rule(tmp_path, name, problems):
+    """What the rule program `name` prints for each of the problems."""
+    exe = str(tmp_path / name)
+    _gxx(exe, [os.path.join(NATIVE, name + ".cpp")])
+    text = "\n".join(" ".join(map(str, s)) for s in problems)
+    r = subprocess.run([exe], input=text, capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stderr
+    out = [tuple(map(int, ln.split())) for ln in r.stdout.splitlines()]
+    assert len(out) == len(problems)
+    return out
+
+
+def test_topk_threads_where_fewer_are_slower(tmp_path):
+    """S, q_offset, block_q, k, window -> threads: problems measured slower with
+    fewer threads (many positions to write, few rows with any to choose), and the
+    ones fewer threads are for."""
+    want = {(4096, 0, 1, 4080, 0): 512, (4096, 2560, 1, 4080, 0): 512,
+            (2048, 0, 1, 2032, 0): 512, (8192, 7680, 1, 2048, 0): 512,
+            (16384, 15872, 1, 2048, 0): 512, (16384, 15872, 1, 64, 128): 512,
+            (8192, 4096, 1, 6144, 0): 256, (4096, 0, 1, 3072, 0): 256,
+            (2048, 0, 1, 64, 0): 128, (4096, 0, 1, 2560, 0): 128, (8192, 0, 1, 2048, 0): 128,
+            (4096, 0, 1, 512, 0): 64, (16384, 0, 1, 2048, 0): 256,
+            (32768, 0, 64, 2048, 128): 512, (100, 0, 64, 2_000_000_000, 0): 512}
+    got = _rule(tmp_path, "topk_rule", list(want))
+    assert [g for g, in got] == list(want.values()), list(zip(want.items(), got))
+
+
 def test_masked_shapes_take_the_masked_kernel(tmp_path):
     """The shapes of the masked kernel's GPU tests are on its side of the rule, in
     both of its forms, and calls it was measured slower at are not."""
     from test_gpu_next import MASKED
-    exe = str(tmp_path / "mask_rule")
-    _gxx(exe, [os.path.join(NATIVE, "mask_rule.cpp")])
-
-    def rule(shapes):
-        text = "\n".join(" ".join(map(str, s)) for s in shapes)
-        r = subprocess.run([exe], input=text, capture_output=True, text=True, timeout=60)
-        assert r.returncode == 0, r.stderr
-        return [tuple(map(int, ln.split())) for ln in r.stdout.splitlines()]
-
     taken = [s[:2] + s[3:7] for s in MASKED] + [(3000, 0, 64, 16, 128, 1024)]
-    got = rule(taken)
-    assert len(got) == len(taken) and all(m for m, _ in got), list(zip(taken, got))
+    got = _rule(tmp_path, "mask_rule", taken)
+    assert all(m for m, _ in got), list(zip(taken, got))
     assert {(s[4], split) for s, (_, split) in zip(taken, got)} == {
         (64, 0), (64, 1), (128, 0), (128, 1), (256, 0)}
     # 1024 queries at one head a group: 299 us against 219 gathered; rows of 64
     # entries; a support row too long to count in 32 bits
     gathered = [(4096, 3072, 8, 8, 128, 1024), (4096, 3072, 8, 8, 128, 2048),
                 (2048, 0, 32, 8, 128, 64), (64, 0, 1, 1, 64, 2_000_000_000)]
-    assert not any(m for m, _ in rule(gathered))
+    assert not any(m for m, _ in _rule(tmp_path, "mask_rule", gathered))
 
 
 @pytest.mark.parametrize("name", ["dense_chunk_mfma.hip", "sparse_mask_mfma.hip"])
