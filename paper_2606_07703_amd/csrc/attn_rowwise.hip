@@ -9,13 +9,13 @@
 // online-softmax state, with each lane holding d/16 contiguous elements of the
 // head dimension. A key row k[s,g,:] is read by one group as a single coalesced
 // segment (256 B for bf16 at d=128), and the HPW heads of the chunk reuse it
-// from registers. A step loads 2 to 8 keys a group before it uses the first:
-// with one key a step the walk was a chain of load latencies. The partial
-// states are merged with cross-group shuffles, then through LDS.
+// from registers. A step loads 1 to 8 keys a group before it uses the first
+// (row_keys): with one key a step the walk is a chain of load latencies, which
+// many waves hide where the states are small. The partial states are merged
+// with cross-group shuffles, then through LDS.
 //
-// This path serves every shape and dtype; it is also the per-query sparse
-// path, where each query owns its support and there is nothing to share
-// between queries.
+// This path serves every shape and dtype; the matrix-core kernels take the bf16
+// shapes they are built for.
 #include <math.h>
 
 #include "common.hpp"
@@ -26,27 +26,34 @@ namespace {
 
 constexpr float kLazy = 8.f;
 
-// Keys a group takes per step: as many K and V rows as fit in 64 registers,
-// all loaded before the first is used (one where four heads of 256 leave no
-// more room for a second wave on the SIMD).
-template <int D, int HPW>
-constexpr int row_keys() {
-  if (HPW == 1) return D == 64 ? 4 : 1;   // small states: more waves hide the latency
-  return D == 64 ? 8 : D == 128 ? 4 : HPW == 4 ? 1 : 2;
+// Keys a group takes per step, all loaded before the first is used: what was the
+// fastest over lists of 8 to 512 keys (supports; many: k >= 256) and 300 to 2500
+// keys (dense). One head of 128 or 256, and supports at d = 256, stay at one: their
+// registers are better spent on waves.
+template <int D, int HPW, bool SPARSE>
+constexpr int row_keys(bool many) {
+  if (SPARSE && D == 64) return HPW == 1 ? 2 : many ? 4 : 1;
+  if (SPARSE) return D == 128 && HPW == 4 ? 2 : 1;
+  if (D == 64) return 4;
+  if (D == 128) return HPW == 1 ? 8 : HPW == 2 ? 2 : 4;
+  return HPW == 1 ? 1 : 2;
 }
 
-// NWK waves share a (query, head chunk): they take the steps in turn.
-template <typename T, int D, int HPW, bool SPARSE, int NWK>
+// NWK waves share a (query, head chunk): they take the steps, of KEYS keys a
+// group, in turn. KEYS = 0: one key a step, its support entry read in the step itself.
+template <typename T, int D, int HPW, bool SPARSE, int NWK, int KEYS>
 __global__ __launch_bounds__(NWK * 64) void attn_rowwise_kernel(
     int S, int Hq, int Hkv, int G, float scale_log2, const T *__restrict__ q,
     const T *__restrict__ k, const T *__restrict__ v, const int32_t *__restrict__ idx, int kk,
     int b, size_t gstride, T *__restrict__ o, float *__restrict__ lse, KvPages pages, int qo) {
   // q, o and lse are addressed by position: the host shifts them back by qo rows
-  constexpr int EPL = D / 16, U = row_keys<D, HPW>();
+  constexpr int EPL = D / 16, U = KEYS > 0 ? KEYS : 1;
   const int t = qo + blockIdx.x;
   const int h0 = blockIdx.y * HPW;
   const int j = h0 / G;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  // in a scalar register: the loop's counter and branches are then scalar
+  const int wave = NWK > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   const int grp = lane >> 4;
   const int sub = lane & 15;
 
@@ -68,67 +75,99 @@ __global__ __launch_bounds__(NWK * 64) void attn_rowwise_kernel(
 
   const int n = SPARSE ? kk : t + 1;
   const int32_t *ir = SPARSE ? idx + (size_t)j * gstride + (size_t)((t - qo) / b) * kk : nullptr;
-  // the support entries of a step are loaded during the step before
   auto entry = [&](int base, int u) {
     const int i = base + 4 * u + grp;
     return SPARSE ? (i < n ? ir[i] : -1) : i;
   };
-  int next[U];
+  // The running max moves only when a logit exceeds it by 2^kLazy, so the
+  // accumulator is rescaled rarely (probabilities stay <= 2^kLazy).
+  auto raise = [&](int hh, float top) {
+    if (top > m[hh] + kLazy) {
+      const float corr = __builtin_amdgcn_exp2f(m[hh] - top);  // m = -inf gives 0
+      l[hh] *= corr;
 #pragma unroll
-  for (int u = 0; u < U; ++u) next[u] = entry(wave * 4 * U, u);
-  for (int base = wave * 4 * U; base < n; base += NWK * 4 * U) {
-    int s[U];
-    bool valid[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {   // entry base + 4 u + grp
-      s[u] = next[u];
-      valid[u] = s[u] < n;
-      next[u] = entry(base + NWK * 4 * U, u);
+      for (int e = 0; e < EPL; ++e) acc[hh][e] *= corr;
+      m[hh] = top;
     }
-    if (SPARSE) {
+  };
+  auto add = [&](int hh, float x, const float (&vf)[EPL]) {
+    const float pr = __builtin_amdgcn_exp2f(x - m[hh]);
+    l[hh] += pr;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        valid[u] = s[u] >= 0 && s[u] <= t && s[u] < S;
-        if (valid[u]) {
-          s[u] = pages.row(s[u]);   // the K/V row (identity unless the cache is paged)
-          valid[u] = s[u] >= 0;
+    for (int e = 0; e < EPL; ++e) acc[hh][e] = fmaf(pr, vf[e], acc[hh][e]);
+  };
+  if constexpr (KEYS == 0) {
+    static_assert(NWK == 1, "one wave");
+    for (int base = 0; base < n; base += 4) {
+      int s = entry(base, 0);
+      bool valid = SPARSE ? s >= 0 && s <= t && s < S : s < n;
+      if (SPARSE && valid) {
+        s = pages.row(s);   // the K/V row (identity unless the cache is paged)
+        valid = s >= 0;
+      }
+      if (!valid) s = 0;
+      const size_t row = ((size_t)s * Hkv + j) * D + sub * EPL;
+      float kf[EPL], vf[EPL];
+      load_row<EPL>(k + row, kf);
+      load_row<EPL>(v + row, vf);
+#pragma unroll
+      for (int hh = 0; hh < HPW; ++hh) {
+        float part = 0.f;
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) part = fmaf(qr[hh][e], kf[e], part);
+        const float x = row16_sum(part);
+        if (valid) {
+          raise(hh, x);
+          add(hh, x, vf);
         }
       }
     }
-    float kf[U][EPL], vf[U][EPL];
+  } else {
+    // the support entries of a step are loaded during the step before
+    int next[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const size_t row = ((size_t)(valid[u] ? s[u] : 0) * Hkv + j) * D + sub * EPL;
-      load_row<EPL>(k + row, kf[u]);
-      load_row<EPL>(v + row, vf[u]);
-    }
+    for (int u = 0; u < U; ++u) next[u] = entry(wave * 4 * U, u);
+    for (int base = wave * 4 * U; base < n; base += NWK * 4 * U) {
+      int s[U];
+      bool valid[U];
 #pragma unroll
-    for (int hh = 0; hh < HPW; ++hh) {
-      float x[U], top = -INFINITY;
+      for (int u = 0; u < U; ++u) {   // entry base + 4 u + grp
+        s[u] = next[u];
+        valid[u] = s[u] < n;
+        next[u] = entry(base + NWK * 4 * U, u);
+      }
+      if (SPARSE) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          valid[u] = s[u] >= 0 && s[u] <= t && s[u] < S;
+          if (valid[u]) {
+            s[u] = pages.row(s[u]);   // the K/V row (identity unless the cache is paged)
+            valid[u] = s[u] >= 0;
+          }
+        }
+      }
+      float kf[U][EPL], vf[U][EPL];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        float part = 0.f;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) part = fmaf(qr[hh][e], kf[u][e], part);
-        x[u] = row16_sum(part);
-        if (valid[u]) top = fmaxf(top, x[u]);
-      }
-      // The running max moves only when a logit exceeds it by 2^kLazy, so
-      // the accumulator is rescaled rarely (probabilities stay <= 2^kLazy).
-      if (top > m[hh] + kLazy) {
-        const float corr = __builtin_amdgcn_exp2f(m[hh] - top);  // m = -inf gives 0
-        l[hh] *= corr;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[hh][e] *= corr;
-        m[hh] = top;
+        const size_t row = ((size_t)(valid[u] ? s[u] : 0) * Hkv + j) * D + sub * EPL;
+        load_row<EPL>(k + row, kf[u]);
+        load_row<EPL>(v + row, vf[u]);
       }
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (!valid[u]) continue;   // its row is not the key's: skipped, not weighted by 0
-        const float pr = __builtin_amdgcn_exp2f(x[u] - m[hh]);
-        l[hh] += pr;
+      for (int hh = 0; hh < HPW; ++hh) {
+        float x[U], top = -INFINITY;
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[hh][e] = fmaf(pr, vf[u][e], acc[hh][e]);
+        for (int u = 0; u < U; ++u) {
+          float part = 0.f;
+#pragma unroll
+          for (int e = 0; e < EPL; ++e) part = fmaf(qr[hh][e], kf[u][e], part);
+          x[u] = row16_sum(part);
+          if (valid[u]) top = fmaxf(top, x[u]);
+        }
+        raise(hh, top);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (valid[u]) add(hh, x[u], vf[u]);   // else another's row: skipped, not weighted by 0
       }
     }
   }
@@ -190,40 +229,60 @@ __global__ __launch_bounds__(NWK * 64) void attn_rowwise_kernel(
   }
 }
 
-template <typename T, int D, int HPW, int NWK>
+template <typename T, int D, int HPW, bool SPARSE, int NWK, int U>
 hipError_t launch_w(const Prob &p, const void *q, const void *k, const void *v,
                     const int32_t *idx, void *o, float *lse, hipStream_t st, KvPages pages) {
-  dim3 grid(p.nq, p.Hq / HPW);
-  const float sl2 = p.scale * kLog2e;
   // chunk rows are addressed by position
   const size_t shift = (size_t)p.qo * p.Hq;
-  const T *qs = (const T *)q - shift * D;
-  T *os = o ? (T *)o - shift * D : nullptr;
-  float *ls = lse ? lse - shift : nullptr;
-  if (idx)
-    hipLaunchKernelGGL((attn_rowwise_kernel<T, D, HPW, true, NWK>), grid, dim3(NWK * 64), 0, st,
-                       p.S, p.Hq, p.Hkv, p.G, sl2, qs, (const T *)k, (const T *)v, idx, p.k, p.b,
-                       p.idx_group_stride(), os, ls, pages, p.qo);
-  else
-    hipLaunchKernelGGL((attn_rowwise_kernel<T, D, HPW, false, NWK>), grid, dim3(NWK * 64), 0, st,
-                       p.S, p.Hq, p.Hkv, p.G, sl2, qs, (const T *)k, (const T *)v, nullptr, 0, 1,
-                       (size_t)0, os, ls, KvPages(), p.qo);
+  hipLaunchKernelGGL((attn_rowwise_kernel<T, D, HPW, SPARSE, NWK, U>), dim3(p.nq, p.Hq / HPW),
+                     dim3(NWK * 64), 0, st, p.S, p.Hq, p.Hkv, p.G, p.scale * kLog2e,
+                     (const T *)q - shift * D, (const T *)k, (const T *)v, idx, SPARSE ? p.k : 0,
+                     SPARSE ? p.b : 1, SPARSE ? p.idx_group_stride() : 0,
+                     o ? (T *)o - shift * D : nullptr, lse ? lse - shift : nullptr, pages, p.qo);
   return hipGetLastError();
+}
+
+// Four waves a query where one each would leave the chip short of waves and
+// each gets a step of its own: fp32, one key a step and one wave before, 512
+// tokens at 4/2 heads, d = 64, dense 42.3 -> 15.4 us; 1024 at 8/2, d = 128, k =
+// 512 97 -> 72. Four waves at 8192 queries times heads, d = 128, k = 256: 100 us,
+// one 84. At d = 256 a wave has the registers of two: never for one head, and
+// for supports only long ones (1024 tokens at 4/2 heads, k = 64: 28 us with four
+// waves, 22 with one; k = 256 52 / 65).
+template <typename T, int D, int HPW, bool SPARSE, int U>
+hipError_t launch_u(const Prob &p, const void *q, const void *k, const void *v,
+                    const int32_t *idx, void *o, float *lse, hipStream_t st, KvPages pages) {
+  const int64_t waves = (int64_t)p.nq * (p.Hq / HPW);
+  const int keys = SPARSE ? p.k : p.S;
+  constexpr int least = D < 256 || !SPARSE ? 16 * U : HPW == 2 ? 256 : 64;
+  if constexpr (D < 256 || HPW > 1)
+    if (waves <= 2048 && keys >= least)
+      return launch_w<T, D, HPW, SPARSE, 4, U>(p, q, k, v, idx, o, lse, st, pages);
+  return launch_w<T, D, HPW, SPARSE, 1, U>(p, q, k, v, idx, o, lse, st, pages);
 }
 
 template <typename T, int D, int HPW>
 hipError_t launch_t(const Prob &p, const void *q, const void *k, const void *v,
                     const int32_t *idx, void *o, float *lse, hipStream_t st, KvPages pages) {
-  // Four waves a query where one each would leave the chip short of waves and
-  // each gets a step of its own: fp32, one key a step and one wave before, 512
-  // tokens at 4/2 heads, d = 64, dense 42.3 -> 15.4 us; 1024 at 8/2, d = 128, k =
-  // 512 97 -> 72. Four waves at 8192 queries times heads, d = 128, k = 256: 100
-  // us, one 84.
-  const int64_t waves = (int64_t)p.nq * (p.Hq / HPW);
-  const int keys = idx ? p.k : p.S;
-  if (waves <= 2048 && keys >= 16 * row_keys<D, HPW>())
-    return launch_w<T, D, HPW, 4>(p, q, k, v, idx, o, lse, st, pages);
-  return launch_w<T, D, HPW, 1>(p, q, k, v, idx, o, lse, st, pages);
+  // One head of 128 or 256, one key a step: reading the entry ahead gains 2 to 26%
+  // (2500 tokens at 8/8 heads, d = 128, k = 100 124 -> 101 us), but loses with
+  // long supports where the waves all run at once (1024 at 6/2 heads, k = 512 91 ->
+  // 103), at d = 256 (300 at 6/2, k = 256 53 -> 59) and over long dense rows there.
+  const int64_t waves = (int64_t)p.nq * p.Hq;
+  if constexpr (HPW == 1 && D >= 128) {
+    if (idx && (D == 256 ? p.k >= 256 : p.k >= 64 && waves > 4096 && waves < 8192))
+      return launch_w<T, D, HPW, true, 1, 0>(p, q, k, v, idx, o, lse, st, pages);
+    if (D == 256 && !idx && p.S > 2048)
+      return launch_w<T, D, HPW, false, 1, 0>(p, q, k, v, idx, o, lse, st, pages);
+  }
+  if (!idx)
+    return launch_u<T, D, HPW, false, row_keys<D, HPW, false>(true)>(p, q, k, v, idx, o, lse, st,
+                                                                     pages);
+  if (p.k >= 256)
+    return launch_u<T, D, HPW, true, row_keys<D, HPW, true>(true)>(p, q, k, v, idx, o, lse, st,
+                                                                   pages);
+  return launch_u<T, D, HPW, true, row_keys<D, HPW, true>(false)>(p, q, k, v, idx, o, lse, st,
+                                                                  pages);
 }
 
 template <typename T, int D>

@@ -245,6 +245,38 @@ def test_topk(case):
     assert np.array_equal(got, ref)   # same fp32 values: selection must be bit-exact
 
 
+@pytest.mark.parametrize("S,Hq,Hkv,d,k,b", [
+    # fp32 rows: one, two and four heads a wave; one wave a query and four; lists
+    # of one key, of a step and one either side of it, and not a multiple of one;
+    # the plain walk (700 and 300 rows of one head, 2051 dense)
+    (3, 4, 2, 64, 1, 1), (130, 8, 2, 64, 17, 1), (300, 8, 2, 64, 257, 1), (520, 12, 4, 64, 63, 4),
+    (300, 6, 2, 64, 65, 1), (900, 3, 3, 64, 31, 2), (700, 8, 8, 128, 65, 1), (90, 3, 3, 128, 79, 1),
+    (400, 12, 3, 128, 33, 1), (300, 4, 2, 128, 255, 1), (300, 6, 2, 256, 256, 1),
+    (120, 6, 2, 256, 99, 1), (400, 4, 2, 256, 300, 1), (150, 4, 1, 256, 65, 1),
+    (2051, 3, 3, 256, 5, 16),
+])
+def test_rowwise_walks(S, Hq, Hkv, d, k, b):
+    inp = _inp(S, Hq, Hkv, d, dtype="f32", seed=S + k, peaked=True)
+    table = make_support(S, b, k, seed=k, shuffle=True)
+    table[::3, ::4] = -1
+    table[1::3, ::5] = S
+    p = B.Problem(S, Hq, Hkv, d, topk=k, block_q=b, dtype="f32")
+    q, kk, v = inp.q.cuda(), inp.k.cuda(), inp.v.cuda()
+    o, o2 = torch.full_like(q, 7.0), torch.full_like(q, 7.0)
+    lse = torch.empty(S, Hq, device="cuda")
+    B.sp_sparse_gqa_attn(p, q, kk, v, table.cuda(), o)
+    B.sp_dense_attn(p, q, kk, v, o2, lse)
+    torch.cuda.synchronize()
+    rows = np.unique(np.r_[0:min(S, 40), np.arange(0, S, max(1, S // 60)), S - 1])
+    bad = torch.where(table < S, table, torch.full_like(table, -1))
+    check_attention(f64(o)[rows], oracle.sparse(inp.q, inp.k, inp.v, bad, b, rows=rows),
+                    oracle.sparse(inp.q, inp.k, inp.v.abs(), bad, b, rows=rows), "f32")
+    ref, ref_lse = oracle.dense(inp.q, inp.k, inp.v, rows=rows)
+    check_attention(f64(o2)[rows], ref, oracle.dense(inp.q, inp.k, inp.v.abs(), rows=rows)[0],
+                    "f32")
+    assert max_err(f64(lse)[rows], ref_lse) <= 1e-4 * max(1.0, np.abs(ref_lse).max())
+
+
 @pytest.mark.parametrize("S,qo,b,k,W,kind", [
     # enough rows for each narrower workgroup, at both ends of its lengths:
     # 64 threads (4096 candidates), 128 (8192) and 256 (16384); aligned rows and
