@@ -175,7 +175,7 @@ __device__ __forceinline__ float half_combine(float x, Op op) {
 // column n for queries 8i + 4h + r. A selection block's aggregate is then a
 // lane-local reduction plus one half-wave combine, and the half index h picks
 // which key tile or block a lane stores, so every store row is contiguous.
-template <int DI, int BQ, bool MAXPOS, int NW>
+template <int DI, int BQ, bool MAXPOS, bool CHUNK, int NW>
 __global__ __launch_bounds__(NW * 64) void indexer_block_kernel(int S, int qo, int g0, int n_units,
                                                                 int agg, int relu, float scale,
                                                                 const uint16_t *__restrict__ qi,
@@ -330,7 +330,7 @@ __global__ __launch_bounds__(NW * 64) void indexer_block_kernel(int S, int qo, i
         const int s = kt0 + sb * 64 + v_key(v);
         const int tb0 = qw0_ + v_block(v) * BQ;          // first query of the block
         const int tb1 = min(tb0 + BQ, S) - 1;
-        if (tb0 >= qo && tb0 < S && s <= tb1) Y[(size_t)(tb0 / BQ) * S + s] = o[sb][v];
+        if ((!CHUNK || tb0 >= qo) && tb0 < S && s <= tb1) Y[(size_t)(tb0 / BQ) * S + s] = o[sb][v];
       }
   };
   // Tile wholly below the wave's first query (no masks): its 2 NSUB chains of
@@ -480,7 +480,7 @@ __global__ __launch_bounds__(NW * 64) void indexer_block_kernel(int S, int qo, i
         for (int sb = 0; sb < NSUB; ++sb) {
           const int s = kt0 + sb * 64 + v_key(0);
           const float m = op(out[sb][0], red[wave >> 1][sb * 64 + v_key(0)]);
-          if (tb0 >= qo && tb0 < S && s <= tb1) Y[(size_t)(tb0 / BQ) * S + s] = m;
+          if ((!CHUNK || tb0 >= qo) && tb0 < S && s <= tb1) Y[(size_t)(tb0 / BQ) * S + s] = m;
         }
       }
     }
@@ -493,10 +493,12 @@ __global__ __launch_bounds__(NW * 64) void indexer_block_kernel(int S, int qo, i
     const int group = uc.qg, nt = uc.nt;
     qw0 = group * QG + wave * kQW;
     qw_last = min(qw0 + kQW, S) - 1;
-    if (qw_last < qo) qw_last = -1;   // every query before the chunk: nothing to multiply
+    // every query before the chunk: nothing to multiply
+    if (CHUNK && qw_last < qo) qw_last = -1;
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt) {
-      const int row = max(min(qw0 + qt * 32 + n, S - 1), qo);
+      int row = min(qw0 + qt * 32 + n, S - 1);
+      if constexpr (CHUNK) row = max(row, qo);
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
         a[qt][ks] = as_bf16x8(ldg16(qi + (size_t)row * DI + ks * 16 + h * 8));
@@ -717,20 +719,28 @@ hipError_t launch_di(const Prob &p, const void *qi, const void *ki, float *score
   constexpr int NW = 8, QG = NW * kQW;
   // A chunk starts inside its first 512-query group: that group's queries
   // before it are loaded as the chunk's first row and their blocks are not
-  // stored (qo is a multiple of b, so no block straddles the start).
+  // stored (qo is a multiple of b, so no block straddles the start). Kernels of
+  // their own: the tests and the clamp cost other launches up to 1.6% (8192
+  // tokens, d_idx 128, b = 16: 19.98 -> 20.31 us).
   const int g0 = p.qo / QG;
   float *y = scores - (size_t)(p.qo / p.b) * p.S;
   const long long units = count_units<QG, BlockTile<DI>::KT>(p.S, g0);
   if (units > INT_MAX) return hipErrorInvalidValue;
   const int n_units = (int)units;
   const bool maxpos = p.agg == SP_AGG_MAX && p.iscale >= 0.f;
+  const bool chunk = p.qo % QG != 0;
+#define SP_BLK_T(BQ, MAXPOS, CHUNK)                                                          \
+  err = launch_persistent<indexer_block_kernel<DI, BQ, MAXPOS, CHUNK, NW>>(                  \
+      NW * 64, n_units, st, p.S, p.qo, g0, n_units, p.agg, p.relu, p.iscale, q, k, y)
 #define SP_BLK(BQ)                                                                           \
-  if (maxpos)                                                                                \
-    err = launch_persistent<indexer_block_kernel<DI, BQ, true, NW>>(                         \
-        NW * 64, n_units, st, p.S, p.qo, g0, n_units, p.agg, p.relu, p.iscale, q, k, y);           \
+  if (maxpos && chunk)                                                                       \
+    SP_BLK_T(BQ, true, true);                                                                \
+  else if (maxpos)                                                                           \
+    SP_BLK_T(BQ, true, false);                                                               \
+  else if (chunk)                                                                            \
+    SP_BLK_T(BQ, false, true);                                                               \
   else                                                                                       \
-    err = launch_persistent<indexer_block_kernel<DI, BQ, false, NW>>(                        \
-        NW * 64, n_units, st, p.S, p.qo, g0, n_units, p.agg, p.relu, p.iscale, q, k, y)
+    SP_BLK_T(BQ, false, false)
   hipError_t err;
   switch (p.b) {
     case 16: SP_BLK(16); break;
@@ -739,6 +749,7 @@ hipError_t launch_di(const Prob &p, const void *qi, const void *ki, float *score
     default: SP_BLK(128); break;
   }
 #undef SP_BLK
+#undef SP_BLK_T
   return err;
 }
 
