@@ -223,7 +223,7 @@ int sp_sparse_gqa_attn_paged(const sp_problem *p, const void *q, const void *k_p
  * on those scores (forced window of min(W,k) most recent positions, then
  * score descending / position ascending; ascending rows, -1 padded), without
  * storing the S x S score matrix: scores are recomputed on the matrix cores
- * in each pass of an 8-bit radix select.
+ * in each pass of a radix select of 10 bits a digit.
  * Requires block_q = 1, dtype bf16, index_dim 64/128/256, seq_len <= 65535,
  * index_scale >= 0; otherwise SP_ERR_UNSUPPORTED. q_idx, k_idx: device bf16
  * [S, d_idx]; idx: device int32 [S, k] (output). workspace: device memory of

@@ -91,8 +91,9 @@ bool indexer_topk_supported(const Prob &p);
 size_t indexer_topk_workspace(const Prob &p);
 hipError_t launch_indexer_topk(const Prob &p, const void *qi, const void *ki, int32_t *idx,
                                void *ws, hipStream_t st);
-// The same without a workspace; problems whose workspace would exceed this
-// many bytes are refused by the API.
+// The same for the entry point without a workspace; problems whose workspace
+// would exceed this many bytes are refused by the API. (The kernel works in LDS
+// and uses none in either.)
 constexpr size_t kIndexerTopkStaticBytes = size_t(64) << 20;
 hipError_t launch_indexer_topk_static(const Prob &p, const void *qi, const void *ki,
                                       int32_t *idx, hipStream_t st);

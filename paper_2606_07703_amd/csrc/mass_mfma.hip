@@ -359,7 +359,7 @@ __global__ __launch_bounds__(kNW * 64) void mass32_kernel(
   constexpr int kMaxChunks = (kMaxHkv * kMT * SLOTS + 63) / 64;
   constexpr int kCPW = (kMaxChunks + kNW - 1) / kNW;   // chunks per wave, at most
   const int rows = Hkv * kMT, chunks = (rows * SLOTS + 63) / 64;
-  const uint32_t key_bytes = (uint32_t)Hkv * D * 2;
+  const uint32_t key_bytes = (uint32_t)Hkv * D * 2;   // (the API keeps k below 4 GiB)
   const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(k), (short)0,
                                                     (uint32_t)S * key_bytes, kBufferDword3);
   const uint32_t kt = (uint32_t)(size_t)(__attribute__((address_space(3))) char *)ktile;
@@ -604,11 +604,9 @@ bool mass32_supported(const Prob &p) {
          p.G % hpw == 0 && p.Hkv <= kMaxHkv && (p.b == 1 || p.b % kMT == 0);
 }
 
-// Per-group tables: the aggregates of a block's keys for every group fit LDS,
-// and the keys lie within the kernel's 32-bit offsets.
+// Per-group tables: the aggregates of a block's keys for every group fit LDS.
 bool mass32_groups_supported(const Prob &p) {
-  return (p.b == 1 || p.b * p.Hkv <= mass_aggregates<false, true>()) &&
-         (uint64_t)p.S * p.Hkv * p.d * 2 < (1ull << 32);
+  return p.b == 1 || p.b * p.Hkv <= mass_aggregates<false, true>();
 }
 
 template <int D>

@@ -245,6 +245,30 @@ def test_indexer_project_hidden_states_past_4gib():
         assert ((whole[-tail:] - part).abs() <= 2.0 ** -7 * part.abs() + 1e-4).all()
 
 
+@pytest.mark.parametrize("di,dm", [(64, 1 << 24), (128, 1 << 24), (256, 1 << 23)])
+def test_indexer_project_weights_past_32_bit_offsets(di, dm):
+    # weights past the ring kernel's 32-bit offsets: they are zero but for the
+    # first and last 4096 model columns, so that the call is the oracle's on those
+    S, edge = 67, 4096
+    say(f"project S={S} d_model={dm} d_idx={di}")
+    gen = torch.Generator(device="cuda").manual_seed(di)
+    cut = lambda t: torch.cat([t[..., :edge], t[..., -edge:]], dim=-1).contiguous()
+    x = torch.empty(S, dm, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    w = torch.zeros(2, di, dm, dtype=torch.bfloat16, device="cuda")
+    for part in (w[..., :edge], w[..., -edge:]):
+        part.normal_(std=(2 * edge) ** -0.5, generator=gen)
+    gamma = 1 + 0.1 * torch.randn(di, generator=gen, device="cuda")
+    beta = 0.1 * torch.randn(di, generator=gen, device="cuda")
+    q, k = (torch.empty(S, di, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    B.sp_indexer_project(B.Problem(S, 1, 1, 64, index_dim=di), x, w[0], w[1], gamma, beta, q, k,
+                         pos0=5)
+    torch.cuda.synchronize()
+    rq, rk = oracle.project(cut(x).cpu(), cut(w[0]).cpu(), cut(w[1]).cpu(), gamma.cpu(),
+                            beta.cpu(), pos0=5)
+    _check_proj(q.cpu(), rq)
+    _check_proj(k.cpu(), rk)
+
+
 # ------------------------------------------------------- fused indexer top-k
 def _fused_and_unfused(S, di, k, W, relu, qi, ki):
     p = B.Problem(S, 1, 1, 64, index_dim=di, topk=k, block_q=1, local_window=W, relu=relu)
