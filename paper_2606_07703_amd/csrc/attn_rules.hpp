@@ -12,8 +12,9 @@ namespace sp {
 // many query rows times keys as an unsplit one but loads twice the tile bytes
 // (about 1.4 times the time), so the longest has to be 1.6 times the share.
 // Split against unsplit, 32/8 heads, d = 128: 1024 queries of 8192 keys
-// (ratio 2.1) 171-195 / 253 us, 2048 tokens (2.0) 46 / 51, 4096 at 16/4 heads
-// (2.0) 76 / 95; past the line 3072 tokens (1.3) 94 / 82, 4000 (1.0) 146 / 121.
+// (ratio 2.1) 215 / 307 us, 2048 tokens (2.0) 44 / 50, 4096 at 16/4 heads (2.0) 76
+// / 94; past the line 3072 tokens (1.3) 92 / 82, 4000 (1.0) 144 / 121, 4096 rows of
+// 8192 (1.0) 659 / 619, though 2048 of 4096 (1.3) 172 / 185.
 inline bool few_workgroups(const Prob &p, int TQ) {
   constexpr int kCus = 256;
   const int64_t wgs = (int64_t)((p.nq + TQ - 1) / TQ) * p.Hkv;

@@ -176,13 +176,14 @@ __device__ __forceinline__ void dense_value_kinds(int t0, int end, int j, int Hk
 // SPLIT: see AttnPipe. CHUNK: the queries start at position qo (0 otherwise),
 // and the P V product takes the weights in fp32, as three bf16 parts, where
 // whole sequences round them to bf16: 1024 queries of 8192 keys, 32/8 heads, d =
-// 128, take 215 us so (two parts 174, one key at a time in fp32 3600). A weight of zero still multiplies its V row, and an infinite
-// entry its weight's two parts, so infinite and NaN V entries reach outputs that
-// they should not. Where a chunk's rows come out NaN although their weights are
-// numbers, the workgroup looks its values over: rows before the last such
-// entry of their tiles are computed again from their own keys (dense_rows), unless
-// its dims are NaN anyhow; the others see every such entry, and the dims that
-// hold any become what those sum up to. Whole sequences are left as the tiles make them.
+// 128, take 215 us so (two parts 174, one key at a time in fp32 3600). A weight
+// of zero still multiplies its V row, and an infinite entry each part of its
+// weight, so infinite and NaN V entries reach outputs that they should not. Where
+// a chunk's rows come out NaN although their weights are numbers, the workgroup
+// looks its values over: rows before the last such entry of their tiles are
+// computed again from their own keys (dense_rows), unless its dims are NaN anyhow;
+// the others see every such entry, and the dims that hold any become what those
+// sum up to. Whole sequences are left as the tiles make them.
 template <int D, bool WANT_O, bool SPLIT, bool CHUNK>
 __global__ __launch_bounds__(attn_max_waves<D>() * 64) SP_ATTN_OCCUPANCY(D) void dense_fwd_kernel(
     int S, int qo, int Hq, int Hkv, int G, int TQ, int nqt, float scale_log2,

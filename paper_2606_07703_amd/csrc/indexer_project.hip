@@ -235,13 +235,19 @@ __global__ __launch_bounds__(kPW * 64) void project_kernel(
 // the operand reads are inline so the compiler adds no wait for the direct
 // loads still in flight.
 //
-// Every workgroup takes in (TOK + N) model rows, and that intake is what
-// bounds it (about 10 TB/s over the chip out of the L2s): the host picks the
-// tile by rounds of workgroups times intake. Against 128 tokens x 2 d_idx
-// columns in 32-column stages for every length, d_model 4096, d_idx 128:
-// 4096 tokens (32 x 128 tiles) 91.6 -> 24.7 us, 8192 (64 x 128) 92.4 -> 34.8,
-// 16384 (128 x 128) 94.5 -> 53.1, 32768 (128 x 256) 111.7 -> 97.4; d_idx 256
-// (64 tokens x 512, register staged before): 4096 119 -> 38, 32768 271 -> 176.
+// Every workgroup takes in (TOK + N) model rows, and the host picks the tile by
+// rounds of workgroups times intake, which orders the tiles' times. It is no
+// constant bound: by the times below the intake is 13.7 TB/s over the chip at 4096
+// tokens, 11.6, 10.1 and 8.3 TB/s at 32768. What limits the short launches is not
+// one unit: at 4096 tokens the matrix cores are busy 11% of the cycles, the vector
+// units 20, LDS 13 (no bank conflict), the L2s serve 12.4 TB/s with 85% hits, and
+// a wave waits 39% of its time. Against 128 tokens x 2 d_idx columns in 32-column
+// stages for every length, d_model 4096, d_idx 128, x and W in the caches from the
+// call before: 4096 tokens (32 x 128 tiles) 91.6 -> 24.7 us, 8192 (64 x 128) 92.4 ->
+// 34.8, 16384 (128 x 128) 94.5 -> 53.1, 32768 (128 x 256) 111.7 -> 97.4; d_idx 256
+// (64 tokens x 512, register staged before): 4096 119 -> 38, 32768 271 -> 176. In a
+// layer step, where other stages have used the caches, 32768 tokens take 130 us by
+// either kernel.
 constexpr int kRK = 64;         // model columns per stage
 constexpr int kRW = 8;          // waves
 constexpr int kProjBufferDword3 = 0x00020000;   // raw buffer resource: 32-bit data format

@@ -11,10 +11,11 @@
 // one exponential per element relative to it, which the gradient reuses: the
 // threads' sums are rescaled when they are merged. Against one 1024-thread
 // workgroup a row, scalar loads and an online maximum with a branch per
-// element: 1024 rows of 8192 keys 35.4 -> 18.1 us, of 12000 41.9 -> 30.3, 512 of
-// 16384 26.2 -> 19.1. Longer rows stay with that kernel: 1024 threads of the
-// new one fill a CU just the same and took 77 us against 73 for 1024 rows of
-// 32768, as it reads nothing twice either up to that length.
+// element, P and z in the caches from the call before: 1024 rows of 8192 keys
+// 35.4 -> 18.1 us, of 12000 41.9 -> 30.3, 512 of 16384 26.2 -> 19.1. Longer rows
+// stay with that kernel: 1024 threads of the new one fill a CU just the same and
+// took 77 us against 73 for 1024 rows of 32768, as it reads nothing twice either
+// up to that length.
 //
 // The P log P - P z sum and sum P accumulate in fp64, since the KL of a good
 // student is a small difference of large terms. The mean over rows is a
