@@ -75,9 +75,10 @@ __global__ __launch_bounds__(NWK * 64) void attn_rowwise_kernel(
 
   const int n = SPARSE ? kk : t + 1;
   const int32_t *ir = SPARSE ? idx + (size_t)j * gstride + (size_t)((t - qo) / b) * kk : nullptr;
-  auto entry = [&](int base, int u) {
-    const int i = base + 4 * u + grp;
-    return SPARSE ? (i < n ? ir[i] : -1) : i;
+  // (a list may hold up to 2^31 - 1 entries, and a step ends past them)
+  auto entry = [&](uint32_t base, int u) {
+    const uint32_t i = base + 4 * u + grp;
+    return SPARSE ? (i < (uint32_t)n ? ir[i] : -1) : (int)i;
   };
   // The running max moves only when a logit exceeds it by 2^kLazy, so the
   // accumulator is rescaled rarely (probabilities stay <= 2^kLazy).
@@ -98,7 +99,7 @@ __global__ __launch_bounds__(NWK * 64) void attn_rowwise_kernel(
   };
   if constexpr (KEYS == 0) {
     static_assert(NWK == 1, "one wave");
-    for (int base = 0; base < n; base += 4) {
+    for (uint32_t base = 0; base < (uint32_t)n; base += 4) {
       int s = entry(base, 0);
       bool valid = SPARSE ? s >= 0 && s <= t && s < S : s < n;
       if (SPARSE && valid) {
@@ -127,7 +128,7 @@ __global__ __launch_bounds__(NWK * 64) void attn_rowwise_kernel(
     int next[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) next[u] = entry(wave * 4 * U, u);
-    for (int base = wave * 4 * U; base < n; base += NWK * 4 * U) {
+    for (uint32_t base = wave * 4 * U; base < (uint32_t)n; base += NWK * 4 * U) {
       int s[U];
       bool valid[U];
 #pragma unroll
