@@ -86,7 +86,7 @@ struct MaskedKeys {
   }
   // After the first fill: whether to gather (the same for the whole workgroup).
   __device__ __forceinline__ bool leave() const {
-    return __builtin_amdgcn_readfirstlane(*seen) * 4 <= few;
+    return __builtin_amdgcn_readfirstlane(*seen) <= few >> 2;   // (one entry in four is seen)
   }
   // Bits of the segment that starts at key tile tile0. (query, 8-entry piece)
   // items, two of a thread's in flight; entries of a piece that share a word
@@ -166,7 +166,7 @@ struct MaskedKeys {
         usable = 0;
         __syncthreads();
         const bool gone =
-            __builtin_amdgcn_readfirstlane(*seen) * 4 <= few * ((float)(U * NT / 2) / items);
+            __builtin_amdgcn_readfirstlane(*seen) <= few * ((float)(U * NT / 8) / items);
         __syncthreads();   // every wave has read it
         if (gone) return;
       }
